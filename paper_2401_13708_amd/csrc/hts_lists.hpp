@@ -1,0 +1,38 @@
+// hts_lists.hpp -- index arithmetic of the lists between the two phases of the
+// Barnes-Hut traversal (also compiled for the host by the tests).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace hts {
+
+// the cells a chunk holds on average at most
+constexpr int kCells = 8;
+
+// a cell handed over (its children are walked for the lanes that rejected
+// it), and a chunk of cells: its number, the block's first query, its first cell's
+// place behind kCells cells for every chunk before it, and its cells and queries.
+// Chunks are numbered below 2^31 (512 bytes of partials each), cells are not (2^31
+// of them are 335544 query blocks at the default list): places are 64 bits wide,
+// and a chunk keeps what distinguishes its own, less than a wave's share.
+struct alignas(16) Cell {
+    int32_t node, next;
+    uint64_t mask;
+};
+struct alignas(16) Chunk {
+    int32_t id, q0, first;
+    uint16_t cells, cnt;
+};
+
+// Chunk `number` of the phase-A wave whose chunks have the numbers from id0 on; its
+// cells are those from `start` on of the wave's.
+__host__ __device__ inline Chunk chunk_of(int id0, int number, int q0, int start, int end, int cnt) {
+    return Chunk{id0 + number, q0, start - number * kCells, (uint16_t)(end - start), (uint16_t)cnt};
+}
+// The place of a phase-A wave's first cell, and of a chunk's.
+__host__ __device__ inline int64_t wave_cells(int id0) { return (int64_t)id0 * kCells; }
+__host__ __device__ inline int64_t chunk_cells(int id, int first) { return (int64_t)id * kCells + first; }
+
+}  // namespace hts

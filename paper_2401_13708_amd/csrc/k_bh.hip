@@ -38,6 +38,7 @@
 // coordinates for the first part of the h-SNE gradient (Sec. 4-C), which walks
 // the same tree with Euclidean node records.
 #include "hts_impl.hpp"
+#include "hts_lists.hpp"
 #include "hts_math.hpp"
 
 namespace hts {
@@ -49,10 +50,9 @@ constexpr int kTopDepth = 1;   // phase A splits each query block's walk at this
 constexpr int kTopSlots = 1 << (2 * kTopDepth);  // ... over this many waves
 
 // Chunks of cells one phase-A wave can hand to phase B at the default
-// item-list size (kListItems), and the cells a chunk holds on average at most.
+// item-list size (kListItems).
 constexpr int kListItems = 256;
 constexpr int kChunks = 200;
-constexpr int kCells = 8;
 // a chunk closes at this many points (or at S, when that is less); one of at
 // least so many is long
 constexpr int kChunkPoints = 128;
@@ -66,17 +66,6 @@ static inline int chunks_of(int list_items) {
     const int64_t l = list_items < kListItems ? list_items : kListItems;
     return (int)((l * kChunks + kListItems - 1) / kListItems);
 }
-
-// a cell handed over (its children are walked for the lanes that rejected
-// it), and a chunk of cells: its number, the block's first query and queries
-struct alignas(16) Cell {
-    int32_t node, next;
-    uint64_t mask;
-};
-struct alignas(16) Chunk {
-    int32_t id, q0, first;
-    uint16_t cells, cnt;
-};
 
 // The chunk lists between the phases, in parts.  Partials sit at fixed places
 // (phase-A wave g owns the chunks from g share on), whatever the order of the
@@ -145,7 +134,7 @@ struct Emit {
         if (points >= kLongPoints) big |= 1ull << (n - 1);
         int end = __shfl_down(starts, 1, kWave);
         if (lane >= n - 1) end = total;
-        const Chunk c{id0 + done + lane, q0, id0 * kCells + starts, (uint16_t)(end - starts), (uint16_t)cnt};
+        const Chunk c = chunk_of(id0, done + lane, q0, starts, end, cnt);
         const uint64_t all = n == kWave ? ~0ull : (1ull << n) - 1, below = (1ull << lane) - 1;
 #pragma unroll
         for (int kind = 0; kind < 2; ++kind) {
@@ -173,7 +162,7 @@ struct Emit {
             first = total;
             points = 0;
         }
-        if (lane == 0) ls.cells[(int64_t)id0 * kCells + total] = Cell{node, next, mask};
+        if (lane == 0) ls.cells[wave_cells(id0) + total] = Cell{node, next, mask};
         ++total;
         points += count;
         return true;
@@ -583,7 +572,7 @@ template <typename T> struct Work {
         : q0(uniform(r.q0)), id(uniform(r.id)), cnt(uniform(r.cnt)), cells(uniform(r.cells)) {
         me = spts[lane < cnt ? q0 + lane : q0];
         q = (int64_t)q0 + lane;
-        if (lane < cells) mine = list[(int64_t)uniform(r.first) + lane];
+        if (lane < cells) mine = list[chunk_cells(id, uniform(r.first)) + lane];
     }
     __device__ __forceinline__ int node(int j) const { return __builtin_amdgcn_readlane(mine.node, j); }
     __device__ __forceinline__ int next(int j) const { return __builtin_amdgcn_readlane(mine.next, j); }
