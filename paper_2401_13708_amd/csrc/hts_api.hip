@@ -370,10 +370,10 @@ __global__ void k_export_nodes(const void *nodes, int dtype, const int32_t *d_m,
     double mx, my;
     if (dtype == HTS_F64) {
         NodeRec<double> r = ((const NodeRec<double> *)nodes)[k];
-        cnt = (int32_t)r.weight; nxd = r.link; mx = r.mx; my = r.my;
+        cnt = r.count; nxd = r.link; mx = r.mx; my = r.my;
     } else {
         NodeRec<float> r = ((const NodeRec<float> *)nodes)[k];
-        cnt = (int32_t)r.weight; nxd = r.link; mx = r.mx; my = r.my;
+        cnt = r.count; nxd = r.link; mx = r.mx; my = r.my;
     }
     if (count) count[k] = cnt;
     if (depth) depth[k] = link_depth(nxd);

@@ -26,23 +26,23 @@ template <> struct alignas(16) PointRec<double> { double x, y, ia, pad; };
 // Node record of the polar quadtree in pre-order, read with scalar loads by
 // the traversal.  link packs the pre-order index after the subtree (low 26
 // bits), the depth (5 bits) and, in the top bit, whether the node is a leaf of
-// several points; a node is a leaf iff next is its own index + 1.  weight is
-// the number of points (exact: below 2^24).  Internal nodes: (mx, my) is the
-// Einstein midpoint, ib = 1 / (1 - |m|^2), c = cosh(r_cell / theta) - 1 (set
-// per theta).  Leaves: (mx, my, ib) is the leaf's first point and c holds the
+// several points; a node is a leaf iff next is its own index + 1.  Internal
+// nodes: (mx, my) is the Einstein midpoint, ib = 1 / (1 - |m|^2), c =
+// cosh(r_cell / theta) - 1 (set per theta).  count is an integer: with a depth cap of
+// 2 or less a tree may hold more than the 2^24 points that a float counts.  Leaves: (mx, my, ib) is the leaf's first point and c holds the
 // position of that point in the sorted order (as an int64 bit pattern, which
 // read as a double is a subnormal: an argument t exceeds it iff t > 0).
 template <typename T> struct NodeRec;
 template <> struct alignas(16) NodeRec<float> {
     float mx, my;
-    float weight;
+    int32_t count;
     uint32_t link;
     double ib;
     double c;
 };
 template <> struct alignas(16) NodeRec<double> {
     double mx, my;
-    float weight;
+    int32_t count;
     uint32_t link;
     double ib;
     double c;

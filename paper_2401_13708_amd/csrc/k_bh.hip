@@ -304,7 +304,7 @@ __device__ __forceinline__ void walk(const NodeRec<T> *__restrict__ nodes,
         if (link & kManyBit) {  // a leaf of several points
             const bool in = __builtin_amdgcn_inverse_ballot_w64(m);
             const int64_t first = (int64_t)__double_as_longlong(cur.c);
-            const int cnt = uniform((int)cur.weight);
+            const int cnt = uniform(cur.count);
             for (int a = 0; a < cnt; ++a) {
                 const PointRec<T> o = spts[first + a];
                 const bool use = in && (first + a) != q;
@@ -334,7 +334,7 @@ __device__ __forceinline__ void walk(const NodeRec<T> *__restrict__ nodes,
         const double t = Geo<MET>::arg(me, cur.mx, cur.my, cur.ib, dd);
         const uint64_t am = __builtin_amdgcn_ballot_w64(!(t <= cur.c)) & m;  // a NaN stays visible
         const uint64_t rej = m & ~am;
-        Part<T> p = part_of<T>(me, cur.mx, cur.my, cur.ib, (T)cur.weight);
+        Part<T> p = part_of<T>(me, cur.mx, cur.my, cur.ib, (T)cur.count);
         pin(p.ux);
         pin(p.uy);
         if (MET == 0) pin(p.ib);
@@ -347,12 +347,12 @@ __device__ __forceinline__ void walk(const NodeRec<T> *__restrict__ nodes,
             } else {
                 c.test += __popcll(m);
                 c.acc += um;
-                c.cover += (unsigned long long)um * (unsigned)cur.weight;
+                c.cover += (unsigned long long)um * (unsigned)cur.count;
             }
             c.work += am != 0;
         }
         int next = rej ? k + 1 : over;
-        if (EMIT && rej && over != k + 1 && em.take(lane, k, over, rej, uniform((int)cur.weight)))
+        if (EMIT && rej && over != k + 1 && em.take(lane, k, over, rej, uniform(cur.count)))
             next = over;
         k = next;
         cur = node_at(nodes, k);
@@ -464,8 +464,8 @@ __device__ __forceinline__ void top_walks(const NodeRec<T> *__restrict__ nodes, 
             const double t = Geo<MET>::arg(me, A.mx, A.my, A.ib, dd);
             acc = t > A.c;
             if (acc && owner)
-                z += (double)((T)A.weight *
-                              Geo<MET>::repel(me, part_of<T>(me, A.mx, A.my, A.ib, (T)A.weight), t, dd, fx, fy));
+                z += (double)((T)A.count *
+                              Geo<MET>::repel(me, part_of<T>(me, A.mx, A.my, A.ib, (T)A.count), t, dd, fx, fy));
         }
         const uint64_t rej = __ballot(in && !acc);
         if (STATS && owner) {
@@ -474,7 +474,7 @@ __device__ __forceinline__ void top_walks(const NodeRec<T> *__restrict__ nodes, 
             c.acc += __popcll(am);
             c.step += 1;
             c.work += am != 0;
-            c.cover += (unsigned long long)__popcll(am) * (unsigned)A.weight;
+            c.cover += (unsigned long long)__popcll(am) * (unsigned)A.count;
         }
         m = rej;
         if (!m) break;

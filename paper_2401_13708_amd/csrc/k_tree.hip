@@ -583,7 +583,7 @@ __global__ __launch_bounds__(kBlock) void k_emit(const uint64_t *__restrict__ ke
     const int32_t count = (int32_t)(end - i);
     const int32_t next = end < n ? node_start[end] : M;
     NodeRec<T> rec;
-    rec.weight = (float)count;
+    rec.count = count;
     rec.link = (uint32_t)next | ((uint32_t)l << kNextBits) | (leaf && count > 1 ? kManyBit : 0u);
     if constexpr (sizeof(T) == 8) rec.pad = 0.0;
     if (leaf && count == 1) {
@@ -801,7 +801,7 @@ __global__ __launch_bounds__(kBlock) void k_emit_euclid(NodeRec<T> *__restrict__
         nodes[k].c = node_threshold(r_cell[k], theta);
         const int l = link_depth(rec.link);
         const int64_t i = node_first[k];
-        const int64_t end = i + (int64_t)rec.weight;
+        const int64_t end = i + rec.count;
         const DD2 se = psum[end], si = psum[i];
         double c[2];
 #pragma unroll
@@ -809,7 +809,7 @@ __global__ __launch_bounds__(kBlock) void k_emit_euclid(NodeRec<T> *__restrict__
             double sm, e;
             two_sum(se.hi[a], -si.hi[a], sm, e);
             e += se.lo[a] - si.lo[a];
-            c[a] = (sm + e) / (double)rec.weight;
+            c[a] = (sm + e) / (double)rec.count;
         }
         rec.mx = (T)c[0];
         rec.my = (T)c[1];
