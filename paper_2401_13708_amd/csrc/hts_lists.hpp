@@ -35,4 +35,24 @@ __host__ __device__ inline Chunk chunk_of(int id0, int number, int q0, int start
 __host__ __device__ inline int64_t wave_cells(int id0) { return (int64_t)id0 * kCells; }
 __host__ __device__ inline int64_t chunk_cells(int id, int first) { return (int64_t)id * kCells + first; }
 
+// The lists are kept in kGroups parts of entries(p) entries: take(p, i) for those
+// that taker w of `takers` takes.  own: each part has as many takers of its
+// own (own_parts(takers)), and w serves one part.  Else the parts' entries are dealt out one after another, on
+// from part to part: were each part's begun with the first taker again, as many
+// takers as the longest part has entries would take nearly all of them (n = 70000 near
+// the rim: 3.3 ms for the gradient on 1000 workgroups of 4 waves, 1.2 dealt on).
+constexpr int kGroups = 64;
+__host__ __device__ inline bool own_parts(int64_t takers) { return takers % kGroups == 0; }
+template <typename N, typename F>
+__host__ __device__ inline void deal(bool own, int64_t w, int64_t takers, N entries, F take) {
+    const int p0 = own ? (int)(w % kGroups) : 0, p1 = own ? p0 + 1 : kGroups;
+    const int64_t stride = own ? takers / kGroups : takers;
+    int64_t i = own ? w / kGroups : w;
+    for (int p = p0; p < p1; ++p) {
+        const int64_t n = entries(p);
+        for (; i < n; i += stride) take(p, i);
+        i -= n;
+    }
+}
+
 }  // namespace hts

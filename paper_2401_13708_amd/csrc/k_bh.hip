@@ -60,7 +60,7 @@ constexpr int kLongPoints = 96;
 // The chunk lists are kept in kGroups parts (the waves of query block b append
 // to part b mod kGroups), long and short chunks apart, each with a counter on
 // a cache line of its own: the waves' atomics on one counter would serialise.
-constexpr int kGroups = kBhCounts / 2;
+static_assert(kBhCounts == 2 * kGroups && kGroups == kWave, "counters; a part a lane");
 
 static inline int chunks_of(int list_items) {
     const int64_t l = list_items < kListItems ? list_items : kListItems;
@@ -84,18 +84,27 @@ struct Lists {
         return chunks + (kind * kGroups + p) * part;
     }
     // f(chunk) for the chunks that wave w of `waves` takes: long ones first,
-    // so that the launch does not end on the longest walks
-    template <typename F>
+    // so that the launch does not end on the longest walks (OWN: the waves are
+    // known to be whole sets)
+    template <bool OWN = false, typename F>
     __device__ __forceinline__ void each(int64_t w, int64_t waves, F f) const {
-        const bool whole = waves % kGroups == 0;  // every part has its own waves
-        const int p0 = whole ? (int)(w % kGroups) : 0, p1 = whole ? p0 + 1 : kGroups;
-        const int64_t stride = whole ? waves / kGroups : waves;
-        for (int p = p0; p < p1; ++p) {
-            const int64_t nl = (int64_t)(uint32_t)uniform((int)counter(0, p));
-            const int64_t ns = (int64_t)(uint32_t)uniform((int)counter(1, p));
-            for (int64_t i = whole ? w / kGroups : w; i < nl + ns; i += stride)
-                f(i < nl ? list(0, p)[i] : list(1, p)[i - nl]);
-        }
+        // every part's length at once where the wave goes through them all
+        int all[2] = {};
+        const int lane = (int)(threadIdx.x & (kWave - 1));
+        const bool own = OWN || own_parts(waves);
+        if (!own)
+            for (int kind = 0; kind < 2; ++kind) all[kind] = (int)counter(kind, lane);
+        int64_t nl = 0;
+        auto length = [&](int kind, int p) {
+            return (int64_t)(own ? uniform((int)counter(kind, p)) : __builtin_amdgcn_readlane(all[kind], p));
+        };
+        deal(
+            own, w, waves,
+            [&](int p) {
+                nl = length(0, p);
+                return nl + length(1, p);
+            },
+            [&](int p, int64_t i) { f(i < nl ? list(0, p)[i] : list(1, p)[i - nl]); });
     }
 };
 
@@ -676,7 +685,7 @@ __device__ __forceinline__ void part_walks(PartLds<WAVES> &lds, const NodeRec<fl
     if (threadIdx.x == 0) s.done = 0;
     __syncthreads();
     int turn = 0;  // of the chunk's first part
-    ls.each(block, item_blocks, [&](const Chunk &r) {
+    ls.each<true>(block, item_blocks, [&](const Chunk &r) {
         const Work<T> k(r, ls.cells, spts, lane);
         int total = 0;
         for (int j = 0; j < k.cells; ++j) total += k.next(j) - k.node(j) - 1;
@@ -1115,9 +1124,10 @@ static void launch_walks(hts_ctx ctx, hipStream_t st, hts_tree t, int64_t n, con
     const int takers = parts ? 1 : wpb;  // waves of a workgroup that take a chunk each
     int64_t gi = ctx->items_grid > 0 ? (int64_t)ctx->items_grid
                                      : cdiv(cdiv(nqb, kGroups) * kTopSlots * 12, takers) * kGroups;
-    const int64_t most = cdiv(nw * a.ls.share, takers);
+    // (no more than take a chunk each, in whole sets: a set a part)
+    const int64_t most = cdiv(cdiv(nw * a.ls.share, takers), kGroups) * kGroups;
     if (gi > most) gi = most;
-    if (gi < 1) gi = 1;  // an empty list (nothing can be handed over)
+    if (gi < 1) gi = ctx->items_grid > 0 ? 1 : kGroups;  // an empty list (nothing can be handed over)
     {
         TimedScope ts(ctx, st, HTS_K_TRAVERSE);
         const int64_t top_blocks = cdiv(nw, kBlock / kWave);

@@ -1,0 +1,49 @@
+"""The traversal's settings (launch shape, list size, cell size) away from their
+defaults: what the launches do differently, and the FP64 oracle's gradient."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2401_13708_amd import hts, synth
+from gpu_inputs import embedding, rel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def settings(ctx):
+    yield ctx
+    ctx.set_item_points(hts.DEFAULT_ITEM_POINTS)
+    ctx.set_item_list(hts.DEFAULT_ITEM_LIST)
+    ctx.set_traversal_launch()
+
+
+def _run(ctx, Y, csr):
+    dev = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (Y, *csr)]
+    tree = hts.Tree(ctx, Y.shape[0], 20)
+    hts.build_polar_tree(ctx, dev[0], tree)
+    st = torch.zeros(hts.STATS_PER_CALL, dtype=torch.int64, device="cuda")
+    g, z = hts.gradient_bh(ctx, *dev, tree, 0.5, 12.0, stats=st)
+    g2, z2 = hts.gradient_bh(ctx, *dev, tree, 0.5, 12.0)
+    torch.cuda.synchronize()
+    assert ctx.check() == 0
+    tree.close()
+    assert torch.equal(g, g2) and torch.equal(z, z2)
+    return g, z, st
+
+
+def _csr(n, dtype):
+    return synth.random_csr(n, min(20, max(1, n // 4)), seed=3, dtype=dtype)
+
+
+# waves that are whole sets of one for each part of the lists, and others
+@pytest.mark.parametrize("n", [300, 13000])
+def test_results_do_not_depend_on_the_launch_shape(settings, n):
+    ctx = settings
+    Y, csr = embedding(n, "late", np.float32), _csr(n, np.float32)
+    want = _run(ctx, Y, csr)
+    for shape in [(1, 1), (63, 1), (64, 1), (65, 2), (1000, 1), (1000, 4), (65537, 1)]:
+        ctx.set_traversal_launch(*shape)
+        for a, b in zip(_run(ctx, Y, csr), want):
+            assert torch.equal(a, b), shape

@@ -47,3 +47,42 @@ def test_a_chunk_is_read_where_its_cells_were_written(tmp_path, nqb, share):
                 }
             }
     }""" % (nqb, share))
+
+
+# takers: the automatic grids, one per chunk where the list is short, and any
+# launch shape that is asked for
+@pytest.mark.parametrize("takers", [1, 2, 63, 64, 65, 128, 1000, 4096, 5000, 30632, 40000, 65537])
+@pytest.mark.parametrize("most", [0, 1, 9, 504, 3000])
+def test_chunks_are_dealt_out_evenly(tmp_path, takers, most):
+    _run(tmp_path, """
+    const int takers = %d, most = %d;
+    int n[kGroups], sum = 0;
+    std::vector<std::vector<int>> seen(kGroups);
+    for (int p = 0; p < kGroups; ++p) {
+        n[p] = (int)((unsigned)(p * 2654435761u) %% (unsigned)(most + 1));
+        seen[p].assign(n[p], 0);
+        sum += n[p];
+    }
+    int longest = 0, largest = 0;
+    for (int w = 0; w < takers; ++w) {
+        int own = 0, part = 0;
+        long long last = -1;
+        deal(own_parts(takers), w, takers, [&](int p) -> int64_t { return n[p]; }, [&](int p, int64_t i) {
+            if (p == part && i <= last) std::printf("order\\n");
+            part = p;
+            last = i;
+            seen[p][i] += 1;
+            ++own;
+        });
+        longest = own > longest ? own : longest;
+    }
+    for (int p = 0; p < kGroups; ++p) {
+        largest = n[p] > largest ? n[p] : largest;
+        for (int s : seen[p])
+            if (s != 1) { std::printf("part %%d: taken %%d times\\n", p, s); return 1; }
+    }
+    // no more than a fair share (of the largest part, where the parts have their own)
+    const int bound = own_parts(takers) ? (largest + takers / kGroups - 1) / (takers / kGroups)
+                                        : (sum + takers - 1) / takers;
+    if (longest > bound) { std::printf("%%d of %%d chunks for one, share %%d\\n", longest, sum, bound); return 1; }
+    """ % (takers, most))
