@@ -47,3 +47,22 @@ def test_results_do_not_depend_on_the_launch_shape(settings, n):
         ctx.set_traversal_launch(*shape)
         for a, b in zip(_run(ctx, Y, csr), want):
             assert torch.equal(a, b), shape
+
+
+# a wave whose share is full goes on without offering cells; the share fills with
+# chunks (lists of 1 and 7) or with cells (small ones)
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("item_list,item_points", [(0, 288), (1, 288), (1, 3), (2, 20), (7, 288), (7, 60)])
+def test_lists_that_run_out(settings, item_list, item_points, dtype):
+    ctx, n = settings, 5000
+    ctx.set_item_list(item_list)
+    ctx.set_item_points(item_points)
+    Y, csr = embedding(n, "late", dtype), _csr(n, dtype)
+    g, z, st = _run(ctx, Y, csr)
+    Yo = Y.astype(np.float64)
+    go, zo, cnt = oracle.gradient_bh(Yo, csr[0], csr[1], csr[2].astype(np.float64), oracle.Tree(Yo, 20), 0.5, 12.0)
+    assert int(st[5]) == n * (n - 1)
+    if dtype == np.float64:
+        assert st[:3].tolist() == [cnt["tests"], cnt["accepts"], cnt["pairs"]]
+    assert rel(g.cpu().numpy(), go) < (1e-10 if dtype == np.float64 else 1e-4)
+    assert float(z) == pytest.approx(zo, rel=1e-10 if dtype == np.float64 else 1e-5)
