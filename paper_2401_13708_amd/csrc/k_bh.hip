@@ -209,7 +209,12 @@ __host__ __device__ inline int item_size(int64_t n, int S) {
 // Phase B alone at n = 2000: 84 and 32.  Parts of 16, 32 or 48 nodes and fewer
 // terms held were not better.  Parts one after another cost 1 to 2 % of a
 // launch (16 jobs of 500 to 20000 points: 305 and 310).
+// Where cells may hold more than kPartsCell points (hts_set_item_points) all are
+// walked whole: a part goes through the links of its cell's nodes before it, so a
+// cell's time grows with the square of its parts (gradient near the rim, n = 12000,
+// in parts and whole: cells of 2048 points 459 and 508 us, of 4096 1301 and 623).
 constexpr int64_t kPartsBelow = 12288, kManyBelow = 6144;
+constexpr int kPartsCell = 2048;
 constexpr int kManyWaves = 8, kFewWaves = 4;
 constexpr int kPartNodes = 24;
 template <typename T> __host__ __device__ inline bool in_parts(int64_t n) {
@@ -1124,8 +1129,10 @@ static void launch_walks(hts_ctx ctx, hipStream_t st, hts_tree t, int64_t n, con
     // phase B: items_grid workgroups of items_waves waves, by default 12
     // waves per phase-A wave (about one per chunk: the hardware hands each
     // freed wave slot the next chunk)
-    int mode = in_parts<T>(kinds * (t->jobs_set ? t->min_job : n)) ? kSomeParts : kNoParts;
-    if (ctx->items_grid == 0 && ctx->items_waves == 1 && in_parts<T>(kinds * n))
+    int mode = kNoParts;
+    const bool short_cells = ctx->item_points <= kPartsCell;
+    if (short_cells && in_parts<T>(kinds * (t->jobs_set ? t->min_job : n))) mode = kSomeParts;
+    if (short_cells && ctx->items_grid == 0 && ctx->items_waves == 1 && in_parts<T>(kinds * n))
         mode = kinds * n < kManyBelow ? kManyWaves : kFewWaves;
     const bool parts = mode > kSomeParts;
     const int wpb = parts ? mode : ctx->items_waves;

@@ -66,3 +66,33 @@ def test_lists_that_run_out(settings, item_list, item_points, dtype):
         assert st[:3].tolist() == [cnt["tests"], cnt["accepts"], cnt["pairs"]]
     assert rel(g.cpu().numpy(), go) < (1e-10 if dtype == np.float64 else 1e-4)
     assert float(z) == pytest.approx(zo, rel=1e-10 if dtype == np.float64 else 1e-5)
+
+
+# cells of more than 2048 points are walked whole, by whatever launch
+@pytest.mark.parametrize("item_points", [2048, 2049, 1 << 20])
+def test_cell_sizes_around_the_largest_walked_in_parts(settings, item_points):
+    ctx, sizes = settings, [5000, 700]
+    ctx.set_item_points(item_points)
+    alone = []
+    for j, n in enumerate(sizes):
+        Y, csr = embedding(n, "late", np.float32, seed=5 + j), _csr(n, np.float32)
+        g, z, st = _run(ctx, Y, csr)
+        Yo = Y.astype(np.float64)
+        go, zo, _ = oracle.gradient_bh(Yo, csr[0], csr[1], csr[2].astype(np.float64), oracle.Tree(Yo, 20), 0.5, 12.0)
+        assert int(st[5]) == n * (n - 1)
+        assert rel(g.cpu().numpy(), go) < 1e-4
+        assert float(z) == pytest.approx(zo, rel=1e-5)
+        alone.append((Y, csr, g, z))
+    # the jobs side by side: the same to the bit
+    (Y0, c0, g0, z0), (Y1, c1, g1, z1) = alone
+    dev = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (
+        np.concatenate([Y0, Y1]), np.concatenate([c0[0], c1[0][1:] + c0[0][-1]]),
+        np.concatenate([c0[1], c1[1] + sizes[0]]).astype(np.int32), np.concatenate([c0[2], c1[2]]))]
+    tree = hts.Tree(ctx, sum(sizes), 20)
+    tree.set_jobs(sizes)
+    hts.build_polar_tree(ctx, dev[0], tree)
+    ex = torch.full((2,), 12.0, dtype=torch.float64, device="cuda")
+    g, z = hts.gradient_bh_jobs(ctx, *dev, tree, ex, 0.5)
+    torch.cuda.synchronize()
+    tree.close()
+    assert torch.equal(g, torch.cat([g0, g1])) and torch.equal(z, torch.cat([z0, z1]))
