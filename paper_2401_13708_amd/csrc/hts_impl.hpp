@@ -61,7 +61,7 @@ constexpr int kBhStats = 6;
 constexpr int kAutoItemPoints = 288;
 // counters of the traversal's work lists (cleared before each traversal), each
 // on a cache line of its own (kCountStride uint32)
-constexpr int kBhCounts = 2 * 64;
+constexpr int kBhCounts = 3 * 64;
 constexpr int kCountStride = 32;
 
 // Job layout as the kernels see it.  Query block qb of job j covers the

@@ -57,10 +57,13 @@ constexpr int kChunks = 200;
 // least so many is long
 constexpr int kChunkPoints = 128;
 constexpr int kLongPoints = 96;
+constexpr int kWholePoints = 32;  // of a chunk that goes to the list kWhole
 // The chunk lists are kept in kGroups parts (the waves of query block b append
-// to part b mod kGroups), long and short chunks apart, each with a counter on
+// to part b mod kGroups), long and short chunks apart, and those of a job in parts that
+// are walked whole all the same, each with a counter on
 // a cache line of its own: the waves' atomics on one counter would serialise.
-static_assert(kBhCounts == 2 * kGroups && kGroups == kWave, "counters; a part a lane");
+constexpr int kLong = 0, kShort = 1, kWhole = 2, kKinds = 3;
+static_assert(kBhCounts == kKinds * kGroups && kGroups == kWave, "counters; a part a lane");
 
 static inline int chunks_of(int list_items) {
     const int64_t l = list_items < kListItems ? list_items : kListItems;
@@ -73,7 +76,7 @@ static inline int chunks_of(int list_items) {
 struct Lists {
     int share;         // chunks a phase-A wave can hand over
     int64_t part;      // entries of one part of one list
-    unsigned *count;   // [long, short][kGroups]
+    unsigned *count;   // [kKinds][kGroups]
     Chunk *chunks;     // likewise
     Cell *cells;
     int *handed;       // per phase-A wave
@@ -83,28 +86,40 @@ struct Lists {
     __device__ __forceinline__ Chunk *list(int kind, int p) const {
         return chunks + (kind * kGroups + p) * part;
     }
-    // f(chunk) for the chunks that wave w of `waves` takes: long ones first,
-    // so that the launch does not end on the longest walks (OWN: the waves are
-    // known to be whole sets)
-    template <bool OWN = false, typename F>
+    // f(chunk, kind) for the chunks of the lists [K0, K1) that wave w of `waves` takes:
+    // long ones first, so that the launch does not end on the longest walks
+    // (OWN: the waves are known to be whole sets)
+    template <int K0, int K1, bool OWN = false, typename F>
     __device__ __forceinline__ void each(int64_t w, int64_t waves, F f) const {
         // every part's length at once where the wave goes through them all
-        int all[2] = {};
+        int all[K1 - K0] = {};
         const int lane = (int)(threadIdx.x & (kWave - 1));
         const bool own = OWN || own_parts(waves);
         if (!own)
-            for (int kind = 0; kind < 2; ++kind) all[kind] = (int)counter(kind, lane);
-        int64_t nl = 0;
-        auto length = [&](int kind, int p) {
-            return (int64_t)(own ? uniform((int)counter(kind, p)) : __builtin_amdgcn_readlane(all[kind], p));
-        };
+            for (int kind = K0; kind < K1; ++kind) all[kind - K0] = (int)counter(kind, lane);
+        int64_t end[K1 - K0];  // of a part's entries of each list, one after another
         deal(
             own, w, waves,
             [&](int p) {
-                nl = length(0, p);
-                return nl + length(1, p);
+                int64_t n = 0;
+#pragma unroll
+                for (int kind = K0; kind < K1; ++kind) {
+                    n += own ? uniform((int)counter(kind, p)) : __builtin_amdgcn_readlane(all[kind - K0], p);
+                    end[kind - K0] = n;
+                }
+                return n;
             },
-            [&](int p, int64_t i) { f(i < nl ? list(0, p)[i] : list(1, p)[i - nl]); });
+            [&](int p, int64_t i) {
+                int kind = K0;
+                int64_t before = 0;
+#pragma unroll
+                for (int a = 0; a + 1 < K1 - K0; ++a)
+                    if (i >= end[a]) {
+                        kind = K0 + a + 1;
+                        before = end[a];
+                    }
+                f(list(kind, p)[i - before], kind);
+            });
     }
 };
 
@@ -127,27 +142,40 @@ template <typename T> struct Walks {
 constexpr int kBoth = 2;
 
 // What a phase-A wave hands over: cells of at most s points, packed in walk
-// order into chunks that close at t points.
+// order into chunks that close at t points.  A cell of fewer nodes than points has
+// leaves of several (depth caps, equal points), which no smaller cell divides: up to
+// `most` points are handed over then, for phase A would walk its leaves one after another
+// (double, n = 3000 in copies of 128, theta = 0: 163 us with cells of 288 points, 300
+// with 64 for all, 94 so; depth cap 8 171, 263 and 113).  And chunks of such cells are not
+// walked in parts, which are even in nodes: a leaf is one wave's whatever its points,
+// and all the next ones wait for it.  They are one cell or kWholePoints (single, a wave a
+// cell, in parts and so: n = 1000 with depth cap 4 60, 76 and 59; n = 6000 in copies of
+// 64, theta = 0, 119, 248 and 122).
 struct Emit {
-    int s, t;
+    int s, t, most;
+    bool parts;          // of a job in parts
     Lists ls;
     int id0, q0, cnt, part;
     int done, n;         // chunks appended to the lists; chunks since
     int total, first;    // cells so far; first cell of the open chunk
-    int points;          // of the open chunk
+    int points, nodes;   // of the open chunk
     int starts;          // lane j: first cell of chunk done + j
-    uint64_t big;        // bit j: chunk done + j is long
+    uint64_t big, whole; // bit j: chunk done + j is long, goes to the list kWhole
+    __device__ __forceinline__ void close() {
+        if (parts && nodes < points) whole |= 1ull << (n - 1);
+        else if (points >= kLongPoints) big |= 1ull << (n - 1);
+    }
     // appends the chunks since the last time (the open one included)
     __device__ __forceinline__ void flush(int lane) {
         if (n == 0) return;
-        if (points >= kLongPoints) big |= 1ull << (n - 1);
+        close();
         int end = __shfl_down(starts, 1, kWave);
         if (lane >= n - 1) end = total;
         const Chunk c = chunk_of(id0, done + lane, q0, starts, end, cnt);
         const uint64_t all = n == kWave ? ~0ull : (1ull << n) - 1, below = (1ull << lane) - 1;
 #pragma unroll
-        for (int kind = 0; kind < 2; ++kind) {
-            const uint64_t m = kind == 0 ? big : all & ~big;
+        for (int kind = 0; kind < kKinds; ++kind) {
+            const uint64_t m = kind == kLong ? big : kind == kWhole ? whole : all & ~(big | whole);
             if (m == 0) continue;
             int at = 0;
             if (lane == 0) at = (int)atomicAdd(&ls.counter(kind, part), (unsigned)__popcll(m));
@@ -156,28 +184,32 @@ struct Emit {
         }
         done += n;
         n = 0;
-        big = 0;
-        points = 0;
+        big = whole = 0;
+        points = nodes = 0;
     }
     // true when the cell was taken; no more will be once the share is full, and
     // the walk ends here (kend) for another to go on
     __device__ __forceinline__ bool take(int lane, int node, int next, uint64_t mask, int count, int &kend) {
-        if (count > s) return false;
-        if (n == 0 || points >= t || total - first == kWave) {
+        const int inside = next - node - 1;
+        const bool shared = inside < count;  // has leaves of several points
+        if (count > s && !(shared && count <= most)) return false;
+        if (n == 0 || points >= (parts && nodes < points ? kWholePoints : t) ||
+            (parts && shared && points + count > s) || total - first == kWave) {
             if (done + n == ls.share) {
                 kend = 0;
                 return false;
             }
             if (n == kWave) flush(lane);
-            if (n && points >= kLongPoints) big |= 1ull << (n - 1);
+            if (n) close();
             starts = lane == n ? total : starts;
             ++n;
             first = total;
-            points = 0;
+            points = nodes = 0;
         }
         if (lane == 0) ls.cells[wave_cells(id0) + total] = Cell{node, next, mask};
         ++total;
         points += count;
+        nodes += inside;
         if (total == ls.share * kCells) kend = 0;
         return true;
     }
@@ -217,6 +249,12 @@ constexpr int64_t kPartsBelow = 12288, kManyBelow = 6144;
 constexpr int kPartsCell = 2048;
 constexpr int kManyWaves = 8, kFewWaves = 4;
 constexpr int kPartNodes = 24;
+// Workgroups that have a chunk of the list kWhole before any has a second one: few chunks
+// have a SIMD of their own, many fill the workgroups that fit on the chip beside their
+// LDS (n = 1000 with depth cap 4, n = 6000 in copies of 64 with theta = 0: 59 and 122 us;
+// all waves of a workgroup first 76 and 128, all workgroups first 59 and 250).
+constexpr int64_t kSpread = 512;
+static_assert(kSpread % kGroups == 0, "whole sets");
 template <typename T> __host__ __device__ inline bool in_parts(int64_t n) {
     return sizeof(T) == 4 && n < kPartsBelow;
 }
@@ -324,8 +362,10 @@ __device__ __forceinline__ void walk(const NodeRec<T> *__restrict__ nodes,
             const bool in = __builtin_amdgcn_inverse_ballot_w64(m);
             const int64_t first = (int64_t)__double_as_longlong(cur.c);
             const int cnt = uniform(cur.count);
+            PointRec<T> ahead = spts[first];
             for (int a = 0; a < cnt; ++a) {
-                const PointRec<T> o = spts[first + a];
+                const PointRec<T> o = ahead;
+                ahead = spts[first + (a + 1 < cnt ? a + 1 : a)];
                 const bool use = in && (first + a) != q;
                 auto term = [&]() {
                     double dd;
@@ -439,7 +479,7 @@ template <typename T, int MET, bool STATS>
 __device__ __forceinline__ void top_walks(const NodeRec<T> *__restrict__ nodes, const Walks<T> &w, int64_t block,
                                           const int32_t *__restrict__ node_start, const Jobs &jb,
                                           const PointRec<T> *__restrict__ spts, int64_t nqb, int S,
-                                          int64_t n) {
+                                          int64_t n, int kinds) {
     const Lists &ls = w.ls;
     T *__restrict__ part0 = w.part0;
     const int64_t g = block * (kBlock / kWave) + uniform((int)(threadIdx.x / kWave));
@@ -458,9 +498,11 @@ __device__ __forceinline__ void top_walks(const NodeRec<T> *__restrict__ nodes, 
     const PointRec<T> me = spts[valid ? q : q0];
     // the job's tree: the pre-order range from its root
     int a = uniform(node_start[jb.off[job]]);
-    const int s = uniform(item_size<T>(jb.off[job + 1] - jb.off[job], S));
-    Emit em{s, s < kChunkPoints ? s : kChunkPoints, ls, (int)(g * ls.share), (int)q0, cnt,
-            (int)(qb % kGroups), 0, 0, 0, 0, 0, 0, 0};
+    const int64_t nj = jb.off[job + 1] - jb.off[job];
+    const int s = uniform(item_size<T>(nj, S));
+    const bool parts = S <= kPartsCell && in_parts<T>(kinds * nj);
+    Emit em{s, s < kChunkPoints ? s : kChunkPoints, S == kAutoItemPoints ? kAutoItemPoints : s, parts, ls,
+            (int)(g * ls.share), (int)q0, cnt, (int)(qb % kGroups), 0, 0, 0, 0, 0, 0, 0, 0, 0};
     T fx = 0, fy = 0;
     double z = 0.0;
     Counters c;
@@ -542,14 +584,14 @@ __global__ __launch_bounds__(kBlock) void k_bh_top(
     const int64_t at = (int64_t)blockIdx.x;
     if constexpr (MET == kBoth) {
         if (at < 2 * top_blocks) {
-            if (at & 1) top_walks<T, 1, STATS>(enodes, b, at >> 1, node_start, jb, spts, nqb, S, n);
-            else top_walks<T, 0, STATS>(nodes, a, at >> 1, node_start, jb, spts, nqb, S, n);
+            if (at & 1) top_walks<T, 1, STATS>(enodes, b, at >> 1, node_start, jb, spts, nqb, S, n, 2);
+            else top_walks<T, 0, STATS>(nodes, a, at >> 1, node_start, jb, spts, nqb, S, n, 2);
         } else {
             both_rows<T>(a, b, at - 2 * top_blocks, row_blocks, perm, pts, rp, col, val, n, err);
         }
     } else {
         if (at < top_blocks) {
-            top_walks<T, MET, STATS>(nodes, a, at, node_start, jb, spts, nqb, S, n);
+            top_walks<T, MET, STATS>(nodes, a, at, node_start, jb, spts, nqb, S, n, 1);
         } else {
             attract_rows<T, kAttractLanes, MET>((at - top_blocks) * kBlock + threadIdx.x, perm, pts, rp, col,
                                                 val, n, a.fattr, err);
@@ -604,8 +646,38 @@ template <typename T> struct Work {
     }
 };
 
-// Phase B: the chunks of small cells, one partial force per lane and one
-// partial Z a chunk.
+// A chunk's result: one partial force per lane and one partial Z.
+template <typename T, bool STATS>
+__device__ __forceinline__ void put_chunk(const Work<T> &k, T fx, T fy, double z, const Counters &c, int lane,
+                                          T *__restrict__ part, double *__restrict__ zitem,
+                                          uint32_t *__restrict__ stats_items) {
+    if (lane < k.cnt) {
+        T *o = part + ((int64_t)k.id * kWave + lane) * 2;
+        o[0] = fx;
+        o[1] = fy;
+    }
+    const double zs = wave_sum(z);
+    if (lane == 0) {
+        zitem[k.id] = zs;
+        put_stats<STATS>(stats_items + (int64_t)k.id * kStats, c);
+    }
+}
+
+// A chunk's cells one after another, by one wave.
+template <typename T, int MET, bool STATS>
+__device__ __forceinline__ void whole_walk(const NodeRec<T> *__restrict__ nodes,
+                                           const PointRec<T> *__restrict__ spts, const Work<T> &k, int lane,
+                                           T &fx, T &fy, double &z, Counters &c) {
+    Emit none{};
+    for (int j = 0; j < k.cells; ++j) {
+        int at = k.node(j) + 1, resume = resume_at(k.mask(j), at);
+        T zw = 0;
+        walk<T, MET, STATS, false, true>(nodes, spts, k.me, k.q, lane, at, k.next(j), resume, none, fx, fy, zw, c);
+        z += (double)zw;
+    }
+}
+
+// Phase B: the chunks of small cells.
 template <typename T, int MET, bool STATS, bool PARTS>
 __device__ __forceinline__ void item_walks(const NodeRec<T> *__restrict__ nodes, const Lists &ls,
                                            T *__restrict__ part, double *__restrict__ zitem,
@@ -615,26 +687,20 @@ __device__ __forceinline__ void item_walks(const NodeRec<T> *__restrict__ nodes,
     const int lane = (int)(threadIdx.x & (kWave - 1));
     const int wpb = (int)(blockDim.x / kWave);
     const int64_t at = block * wpb + uniform((int)(threadIdx.x / kWave));
-    ls.each(at, item_blocks * wpb, [&](const Chunk &r) {
+    ls.each<kLong, PARTS ? kKinds : kWhole>(at, item_blocks * wpb, [&](const Chunk &r, int kind) {
         const Work<T> k(r, ls.cells, spts, lane);
         T fx = 0, fy = 0;
         double z = 0.0;
         Counters c;
-        Emit none{};
         bool parts = false;
         if constexpr (PARTS) {
             const int job = uniform(jb.pjob[k.q0]);
-            parts = in_parts<T>(kinds * (jb.off[job + 1] - jb.off[job]));
+            parts = kind != kWhole && in_parts<T>(kinds * (jb.off[job + 1] - jb.off[job]));
         }
         if (!parts) {
-            for (int j = 0; j < k.cells; ++j) {
-                int at = k.node(j) + 1, resume = resume_at(k.mask(j), at);
-                T zw = 0;
-                walk<T, MET, STATS, false, true>(nodes, spts, k.me, k.q, lane, at, k.next(j), resume, none, fx, fy,
-                                                 zw, c);
-                z += (double)zw;
-            }
+            whole_walk<T, MET, STATS>(nodes, spts, k, lane, fx, fy, z, c);
         } else {
+            Emit none{};
             T sx = 0, sy = 0;  // of the parts before
             double sz = 0.0;
             int b = 0, hi = kPartNodes;  // the cell's first node, the part's end
@@ -667,16 +733,7 @@ __device__ __forceinline__ void item_walks(const NodeRec<T> *__restrict__ nodes,
             fy = sy;
             z = sz;
         }
-        if (lane < k.cnt) {
-            T *o = part + ((int64_t)k.id * kWave + lane) * 2;
-            o[0] = fx;
-            o[1] = fy;
-        }
-        const double zs = wave_sum(z);
-        if (lane == 0) {
-            zitem[k.id] = zs;
-            put_stats<STATS>(stats_items + (int64_t)k.id * kStats, c);
-        }
+        put_chunk<T, STATS>(k, fx, fy, z, c, lane, part, zitem, stats_items);
     });
 }
 
@@ -698,7 +755,7 @@ __device__ __forceinline__ void part_walks(PartLds<WAVES> &lds, const NodeRec<fl
     if (threadIdx.x == 0) s.done = 0;
     __syncthreads();
     int turn = 0;  // of the chunk's first part
-    ls.each<true>(block, item_blocks, [&](const Chunk &r) {
+    ls.each<kLong, kWhole, true>(block, item_blocks, [&](const Chunk &r, int) {
         const Work<T> k(r, ls.cells, spts, lane);
         int total = 0;
         for (int j = 0; j < k.cells; ++j) total += k.next(j) - k.node(j) - 1;
@@ -803,6 +860,15 @@ __device__ __forceinline__ void part_walks(PartLds<WAVES> &lds, const NodeRec<fl
             }
             __syncthreads();
         }
+    });
+    const int64_t b0 = block / kSpread * kSpread, bs = item_blocks - b0 < kSpread ? item_blocks - b0 : kSpread;
+    ls.each<kWhole, kKinds, true>(b0 * WAVES + p * bs + (block - b0), item_blocks * WAVES, [&](const Chunk &r, int) {
+        const Work<T> k(r, ls.cells, spts, lane);
+        T fx = 0, fy = 0;
+        double z = 0.0;
+        Counters c;
+        whole_walk<T, MET, STATS>(nodes, spts, k, lane, fx, fy, z, c);
+        put_chunk<T, STATS>(k, fx, fy, z, c, lane, part, zitem, stats_items);
     });
 }
 
@@ -1060,7 +1126,7 @@ static BhLayout bh_layout(hts_ctx ctx, int64_t nqb, int64_t n, bool stats) {
     sizes[BhLayout::Handed] = nw * 4;
     sizes[BhLayout::Part0] = (size_t)kTopSlots * n * 2 * sizeof(T);
     sizes[BhLayout::Ztop] = nw * 8;
-    sizes[BhLayout::Chunks] = 2 * padded * share * sizeof(Chunk);
+    sizes[BhLayout::Chunks] = kKinds * padded * share * sizeof(Chunk);
     sizes[BhLayout::Cells] = chunks * kCells * sizeof(Cell);
     sizes[BhLayout::Part] = chunks * kWave * 2 * sizeof(T);
     sizes[BhLayout::Zitem] = chunks * 8;
