@@ -63,16 +63,17 @@ def footprint_bytes(n: int, k: int = 90, max_depth: int = 20,
     arrays, its share of the tree storage (60 bytes per node slot, n (depth
     + 1) slots, and 142 bytes per point of keys, sort buffers, prefix sums and
     point records), the per-point buffers of the gradient call, its share of
-    the traversal workspace (four phase-A waves per 64 queries, each with
-    item_list item records of 40 bytes and 64-lane single-precision partials,
-    plus per-slot partials of every query), and 8 MiB for allocation
-    granularity."""
+    the traversal workspace (four phase-A waves per 64 queries, each with 200
+    chunks per 256 of item_list, rounded up: a chunk has a place in three lists of
+    16 bytes, eight cells of 16, a 64-lane single-precision partial and a Z; plus
+    per-slot partials of every query), and 8 MiB for allocation granularity."""
     p = 2 * n * k * 8 + (n + 1) * 8
     state = n * 2 * 4 * 4
     tree = n * (max_depth + 1) * 60 + n * 142
     grad = n * 40
     waves = 4 * (n // 64 + 1)
-    trav = waves * (item_list * (64 * 2 * 4 + 40) + 16) + n * (4 * 2 * 4 + 2 * 4)
+    chunks = -(-min(item_list, 256) * 200 // 256)
+    trav = waves * (chunks * (3 * 16 + 8 * 16 + 64 * 2 * 4 + 8) + 16) + n * (4 * 2 * 4 + 2 * 4)
     return p + state + tree + grad + trav + (8 << 20)
 
 
