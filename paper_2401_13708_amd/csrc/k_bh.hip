@@ -20,7 +20,8 @@
 //     small ones (about 128 points).  The grid holds several times the waves
 //     that fit on the chip, so the hardware hands the next waves (and their
 //     chunks) to whichever SIMD frees up; long chunks come first.
-//     In single precision with few points the waves of a workgroup share a chunk.
+//     In single precision with few points the waves of a workgroup share a chunk,
+//     unless its leaves hold several points.
 // Every chunk writes its own partial force per lane and partial Z at a place
 // that depends on its phase-A wave and its number there; the combine adds, per
 // query block, its waves' partials and chunks in a fixed order, so the result
@@ -466,10 +467,9 @@ __device__ __forceinline__ void both_rows(const Walks<T> &a, const Walks<T> &b, 
 // frontier at depth kTopDepth (its base-4 digits pick the child at each level
 // below the root; a leaf above that depth belongs to the slot whose remaining
 // digits are 0; a slot naming a missing child is idle).  The wave first tests
-// the ancestors of f for its lanes -- a lane that accepts one, or whose
-// rejected ancestor becomes a work item, leaves the walk -- then walks f's
-// subtree.  An ancestor's term, item and counters belong to the one slot whose
-// digits below it are all 0, so every lane meets every cell exactly as in a
+// the ancestors of f for its lanes -- a lane that accepts one leaves the walk --
+// then walks f's subtree, handing over the cells that are small enough.  An
+// ancestor's term and counters belong to the one slot whose digits below it are all 0, so every lane meets every cell exactly as in a
 // single depth-first walk.  These waves are latency-bound chains.  The
 // attractive term (first sum of eq. (15)) runs either in this launch, in the
 // workgroups from top_blocks on, where its waves compete with the chains for
@@ -890,7 +890,7 @@ __global__ __launch_bounds__(MODE == kManyWaves ? kManyWaves * kWave : kBlock) v
         __shared__ PartLds<MODE> s;
         constexpr int kinds = MET == kBoth ? 2 : 1;
         if (at < kinds * item_blocks) {
-            if (MET == 1 || (MET == kBoth && (at & 1)))
+            if (MET == kBoth && (at & 1))
                 part_walks<1, STATS>(s, enodes, b.ls, b.part, b.zitem, b.stats_items, at / kinds, item_blocks, spts);
             else
                 part_walks<0, STATS>(s, nodes, ls, part, zitem, stats_items, at / kinds, item_blocks, spts);
