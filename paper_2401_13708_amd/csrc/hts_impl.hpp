@@ -59,9 +59,9 @@ __host__ __device__ inline int link_depth(uint32_t link) { return (int)(link >> 
 constexpr int kBhStats = 6;
 // hts_set_item_points at this value (the default): sizes chosen per job
 constexpr int kAutoItemPoints = 288;
-// counters of the traversal's work lists (cleared before each traversal), each
-// on a cache line of its own (kCountStride uint32)
-constexpr int kBhCounts = 3 * 64;
+// lines of counters of the traversal's work lists (cleared before each traversal): a
+// cache line (kCountStride uint32) holds one, or two of which the second is rarely used
+constexpr int kBhCounts = 2 * 64;
 constexpr int kCountStride = 32;
 
 // Job layout as the kernels see it.  Query block qb of job j covers the

@@ -60,11 +60,14 @@ constexpr int kChunkPoints = 128;
 constexpr int kLongPoints = 96;
 constexpr int kWholePoints = 32;  // of a chunk that goes to the list kWhole
 // The chunk lists are kept in kGroups parts (the waves of query block b append
-// to part b mod kGroups), long and short chunks apart, and those of a job in parts that
-// are walked whole all the same, each with a counter on
-// a cache line of its own: the waves' atomics on one counter would serialise.
+// to part b mod kGroups), long and short chunks apart, each with a counter on
+// a cache line of its own: the waves' atomics on one counter would serialise.  A third
+// list has the chunks of a job in parts that are walked whole all the same; few
+// trees have any, and its counter follows the long ones' on their line, which every
+// wave reads (gradients of 64 jobs of 500 to 50000 points 1945 us on a line of its own,
+// 1937 so).
 constexpr int kLong = 0, kShort = 1, kWhole = 2, kKinds = 3;
-static_assert(kBhCounts == kKinds * kGroups && kGroups == kWave, "counters; a part a lane");
+static_assert(kBhCounts == 2 * kGroups && kGroups == kWave, "counters; a part a lane");
 
 static inline int chunks_of(int list_items) {
     const int64_t l = list_items < kListItems ? list_items : kListItems;
@@ -77,12 +80,12 @@ static inline int chunks_of(int list_items) {
 struct Lists {
     int share;         // chunks a phase-A wave can hand over
     int64_t part;      // entries of one part of one list
-    unsigned *count;   // [kKinds][kGroups]
-    Chunk *chunks;     // likewise
+    unsigned *count;   // [long and whole, short][kGroups]
+    Chunk *chunks;     // [kKinds][kGroups]
     Cell *cells;
     int *handed;       // per phase-A wave
     __device__ __forceinline__ unsigned &counter(int kind, int p) const {
-        return count[(kind * kGroups + p) * kCountStride];
+        return count[((kind == kShort ? kGroups : 0) + p) * kCountStride + (kind == kWhole ? 1 : 0)];
     }
     __device__ __forceinline__ Chunk *list(int kind, int p) const {
         return chunks + (kind * kGroups + p) * part;
@@ -92,21 +95,25 @@ struct Lists {
     // (OWN: the waves are known to be whole sets)
     template <int K0, int K1, bool OWN = false, typename F>
     __device__ __forceinline__ void each(int64_t w, int64_t waves, F f) const {
-        // every part's length at once where the wave goes through them all
+        // every part's length at once where the wave goes through them all, its own part's
+        // of all lists where it has one
         int all[K1 - K0] = {};
         const int lane = (int)(threadIdx.x & (kWave - 1));
         const bool own = OWN || own_parts(waves);
-        if (!own)
+        if (own) {
+            if (lane < K1 - K0) all[0] = (int)counter(K0 + lane, (int)(w % kGroups));
+        } else {
             for (int kind = K0; kind < K1; ++kind) all[kind - K0] = (int)counter(kind, lane);
+        }
         int64_t end[K1 - K0];  // of a part's entries of each list, one after another
         deal(
             own, w, waves,
             [&](int p) {
                 int64_t n = 0;
 #pragma unroll
-                for (int kind = K0; kind < K1; ++kind) {
-                    n += own ? uniform((int)counter(kind, p)) : __builtin_amdgcn_readlane(all[kind - K0], p);
-                    end[kind - K0] = n;
+                for (int a = 0; a < K1 - K0; ++a) {
+                    n += own ? __builtin_amdgcn_readlane(all[0], a) : __builtin_amdgcn_readlane(all[a], p);
+                    end[a] = n;
                 }
                 return n;
             },
@@ -149,22 +156,28 @@ constexpr int kBoth = 2;
 // (double, n = 3000 in copies of 128, theta = 0: 163 us with cells of 288 points, 300
 // with 64 for all, 94 so; depth cap 8 171, 263 and 113).  And chunks of such cells are not
 // walked in parts, which are even in nodes: a leaf is one wave's whatever its points,
-// and all the next ones wait for it.  They are one cell or kWholePoints (single, a wave a
-// cell, in parts and so: n = 1000 with depth cap 4 60, 76 and 59; n = 6000 in copies of
+// and all the next ones wait for it.  They hold no other cells and close at
+// kWholePoints (single, a wave a cell, in parts and so: n = 1000 with depth cap 4 60, 76 and 59; n = 6000 in copies of
 // 64, theta = 0, 119, 248 and 122).
-struct Emit {
-    int s, t, most;
-    bool parts;          // of a job in parts
+// SHARES: with these rules, for trees that have such cells; the other walks, chains of
+// dependent steps, are spared them and their registers (phase A of 64 jobs of 500 to
+// 50000 points 243 us, 270 with them for all).
+template <bool SHARES> struct Emit {
+    int s, t;
     Lists ls;
     int id0, q0, cnt, part;
+    int most, tw;        // SHARES: as above; where chunks of the list kWhole close (t: there are none)
     int done, n;         // chunks appended to the lists; chunks since
     int total, first;    // cells so far; first cell of the open chunk
-    int points, nodes;   // of the open chunk
+    int points, limit;   // of the open chunk; SHARES: where it closes, t or tw
     int starts;          // lane j: first cell of chunk done + j
     uint64_t big, whole; // bit j: chunk done + j is long, goes to the list kWhole
     __device__ __forceinline__ void close() {
-        if (parts && nodes < points) whole |= 1ull << (n - 1);
-        else if (points >= kLongPoints) big |= 1ull << (n - 1);
+        // (a choice of the mask to change would put both in scratch memory: 2 us a launch)
+        const uint64_t bit = 1ull << (n - 1);
+        const bool to_whole = SHARES && limit != t;
+        if (SHARES) whole |= to_whole ? bit : 0;
+        big |= !to_whole && points >= kLongPoints ? bit : 0;
     }
     // appends the chunks since the last time (the open one included)
     __device__ __forceinline__ void flush(int lane) {
@@ -175,8 +188,8 @@ struct Emit {
         const Chunk c = chunk_of(id0, done + lane, q0, starts, end, cnt);
         const uint64_t all = n == kWave ? ~0ull : (1ull << n) - 1, below = (1ull << lane) - 1;
 #pragma unroll
-        for (int kind = 0; kind < kKinds; ++kind) {
-            const uint64_t m = kind == kLong ? big : kind == kWhole ? whole : all & ~(big | whole);
+        for (int kind = 0; kind < (SHARES ? kKinds : kWhole); ++kind) {
+            const uint64_t m = kind == kLong ? big : kind == kWhole ? whole : all & ~(SHARES ? big | whole : big);
             if (m == 0) continue;
             int at = 0;
             if (lane == 0) at = (int)atomicAdd(&ls.counter(kind, part), (unsigned)__popcll(m));
@@ -186,16 +199,20 @@ struct Emit {
         done += n;
         n = 0;
         big = whole = 0;
-        points = nodes = 0;
+        points = 0;
     }
     // true when the cell was taken; no more will be once the share is full, and
     // the walk ends here (kend) for another to go on
     __device__ __forceinline__ bool take(int lane, int node, int next, uint64_t mask, int count, int &kend) {
-        const int inside = next - node - 1;
-        const bool shared = inside < count;  // has leaves of several points
-        if (count > s && !(shared && count <= most)) return false;
-        if (n == 0 || points >= (parts && nodes < points ? kWholePoints : t) ||
-            (parts && shared && points + count > s) || total - first == kWave) {
+        int here = t;
+        if constexpr (SHARES) {
+            const bool shared = next - node - 1 < count;
+            if (count > s && !(shared && count <= most)) return false;
+            here = shared ? tw : t;
+        } else if (count > s) {
+            return false;
+        }
+        if (n == 0 || points >= (SHARES ? limit : t) || (SHARES && here != limit) || total - first == kWave) {
             if (done + n == ls.share) {
                 kend = 0;
                 return false;
@@ -205,12 +222,12 @@ struct Emit {
             starts = lane == n ? total : starts;
             ++n;
             first = total;
-            points = nodes = 0;
+            points = 0;
+            if (SHARES) limit = here;
         }
         if (lane == 0) ls.cells[wave_cells(id0) + total] = Cell{node, next, mask};
         ++total;
         points += count;
-        nodes += inside;
         if (total == ls.share * kCells) kend = 0;
         return true;
     }
@@ -347,10 +364,10 @@ __device__ __forceinline__ NodeRec<T> node_at(const NodeRec<T> *__restrict__ nod
 // records: their capacity n_max (depth cap + 1) + 1 exceeds any node count).
 // THRU marks the walks of phase B, which run among many waves and are bound
 // by instruction issue: there the term's wave-uniform choice of branch pays.
-template <typename T, int MET, bool STATS, bool EMIT, bool THRU = false, bool HOLD = false>
+template <typename T, int MET, bool STATS, bool EMIT, bool THRU = false, bool HOLD = false, bool SHARES = false>
 __device__ __forceinline__ void walk(const NodeRec<T> *__restrict__ nodes,
                                      const PointRec<T> *__restrict__ spts, const PointRec<T> &me,
-                                     int64_t q, int lane, int &at, int kend, int &resume, Emit &em, T &fx,
+                                     int64_t q, int lane, int &at, int kend, int &resume, Emit<SHARES> &em, T &fx,
                                      T &fy, T &zw, Counters &c, Hold *held = nullptr) {
     int k = at;
     NodeRec<T> cur = node_at(nodes, k);
@@ -501,17 +518,17 @@ __device__ __forceinline__ void top_walks(const NodeRec<T> *__restrict__ nodes, 
     const int64_t nj = jb.off[job + 1] - jb.off[job];
     const int s = uniform(item_size<T>(nj, S));
     const bool parts = S <= kPartsCell && in_parts<T>(kinds * nj);
-    Emit em{s, s < kChunkPoints ? s : kChunkPoints, S == kAutoItemPoints ? kAutoItemPoints : s, parts, ls,
-            (int)(g * ls.share), (int)q0, cnt, (int)(qb % kGroups), 0, 0, 0, 0, 0, 0, 0, 0, 0};
     T fx = 0, fy = 0;
     double z = 0.0;
     Counters c;
     uint64_t m = __ballot(valid);
-    bool live = true;
+    bool live = true, shares = false;
     for (int d = 0; d < kTopDepth; ++d) {
         const NodeRec<T> A = nodes[a];
         const uint32_t nxd = (uint32_t)uniform((int)A.link);
         const int nx = (int)(nxd & kNextMask);
+        // without shared leaves a tree has 1.6 to 2.4 nodes a point
+        if (d == 0 && parts) shares = 5 * (nx - a) < 7 * (int64_t)uniform(A.count);
         // this slot owns node a when its digits below depth d are all 0
         const bool owner = (slot & ((1 << (2 * (kTopDepth - d))) - 1)) == 0;
         if (nx == a + 1) {  // a leaf above the frontier depth: its owner walks it
@@ -550,17 +567,32 @@ __device__ __forceinline__ void top_walks(const NodeRec<T> *__restrict__ nodes, 
         }
         a = ch;
     }
+    int handed = 0;
     if (live && m) {
         const int nxa = (int)((uint32_t)uniform((int)nodes[a].link) & kNextMask);
         T zw = 0;
         int resume = resume_at(m, a);
+        if (ls.share > 0) {
+            const int t = s < kChunkPoints ? s : kChunkPoints;
+            const int tw = !parts ? t : t == kWholePoints ? t + 1 : kWholePoints;
+            const int most = S == kAutoItemPoints ? kAutoItemPoints : s;
+            auto hand_over = [&](auto em) {
+                walk<T, MET, STATS, true>(nodes, spts, me, q, lane, a, nxa, resume, em, fx, fy, zw, c);
+                em.flush(lane);
+                handed = em.done;
+            };
+            // (in double precision two walks would take more registers)
+            if (sizeof(T) == 8 || shares)
+                hand_over(Emit<true>{s, t, ls, (int)(g * ls.share), (int)q0, cnt, (int)(qb % kGroups), most, tw});
+            else if constexpr (sizeof(T) == 4)
+                hand_over(Emit<false>{s, t, ls, (int)(g * ls.share), (int)q0, cnt, (int)(qb % kGroups)});
+        }
         // beyond a full share the walk is one of phase B: with the offers still made,
         // the gradient near the rim at n = 70000 took 2226 us with a list of one, now 1748
-        if (ls.share > 0) walk<T, MET, STATS, true>(nodes, spts, me, q, lane, a, nxa, resume, em, fx, fy, zw, c);
-        if (a < nxa) walk<T, MET, STATS, false, true>(nodes, spts, me, q, lane, a, nxa, resume, em, fx, fy, zw, c);
+        Emit<false> none{};
+        if (a < nxa) walk<T, MET, STATS, false, true>(nodes, spts, me, q, lane, a, nxa, resume, none, fx, fy, zw, c);
         z += (double)zw;
     }
-    em.flush(lane);
     if (valid) {
         part0[((int64_t)slot * n + q) * 2] = fx;
         part0[((int64_t)slot * n + q) * 2 + 1] = fy;
@@ -568,7 +600,7 @@ __device__ __forceinline__ void top_walks(const NodeRec<T> *__restrict__ nodes, 
     const double zs = wave_sum(z);
     if (lane == 0) {
         w.ztop[g] = zs;
-        ls.handed[g] = em.done;
+        ls.handed[g] = handed;
         put_stats<STATS>(w.stats_top + g * kStats, c);
     }
 }
@@ -668,7 +700,7 @@ template <typename T, int MET, bool STATS>
 __device__ __forceinline__ void whole_walk(const NodeRec<T> *__restrict__ nodes,
                                            const PointRec<T> *__restrict__ spts, const Work<T> &k, int lane,
                                            T &fx, T &fy, double &z, Counters &c) {
-    Emit none{};
+    Emit<false> none{};
     for (int j = 0; j < k.cells; ++j) {
         int at = k.node(j) + 1, resume = resume_at(k.mask(j), at);
         T zw = 0;
@@ -700,7 +732,7 @@ __device__ __forceinline__ void item_walks(const NodeRec<T> *__restrict__ nodes,
         if (!parts) {
             whole_walk<T, MET, STATS>(nodes, spts, k, lane, fx, fy, z, c);
         } else {
-            Emit none{};
+            Emit<false> none{};
             T sx = 0, sy = 0;  // of the parts before
             double sz = 0.0;
             int b = 0, hi = kPartNodes;  // the cell's first node, the part's end
@@ -761,7 +793,7 @@ __device__ __forceinline__ void part_walks(PartLds<WAVES> &lds, const NodeRec<fl
         for (int j = 0; j < k.cells; ++j) total += k.next(j) - k.node(j) - 1;
         const int n = (total + kPartNodes - 1) / kPartNodes;
         Counters c;
-        Emit none{};
+        Emit<false> none{};
         int j = 0, b = 0;  // the part's first cell and its first node
         int linked = -1;   // the cell whose links are in
         int links[kLinks];
