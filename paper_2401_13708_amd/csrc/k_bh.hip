@@ -1230,7 +1230,10 @@ static void launch_walks(hts_ctx ctx, hipStream_t st, hts_tree t, int64_t n, con
     int mode = kNoParts;
     const bool short_cells = ctx->item_points <= kPartsCell;
     if (short_cells && in_parts<T>(kinds * (t->jobs_set ? t->min_job : n))) mode = kSomeParts;
-    if (short_cells && ctx->items_grid == 0 && ctx->items_waves == 1 && in_parts<T>(kinds * n))
+    // (cells below a part's size leave the other waves of a workgroup without one: n = 3000
+    // late in a schedule with cells of 8 points 127 us, 116 so)
+    if (short_cells && ctx->item_points >= kPartNodes && ctx->items_grid == 0 && ctx->items_waves == 1 &&
+        in_parts<T>(kinds * n))
         mode = kinds * n < kManyBelow ? kManyWaves : kFewWaves;
     const bool parts = mode > kSomeParts;
     const int wpb = parts ? mode : ctx->items_waves;
