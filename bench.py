@@ -62,10 +62,11 @@ def _src_hash(files):
     return h.hexdigest()[:16]
 
 
-KERNEL_SOURCES = {"traverse": ["k_bh.hip", "hts_math.hpp", "hts_impl.hpp"],
-                  "items": ["k_bh.hip", "hts_math.hpp", "hts_impl.hpp"],
-                  "attract": ["k_grad.hip", "hts_math.hpp", "hts_impl.hpp"],
-                  "tree": ["k_tree.hip", "k_sort.hip", "hts_math.hpp", "hts_impl.hpp"]}
+_HEADERS = ["hts_math.hpp", "hts_term.hpp", "hts_impl.hpp"]
+KERNEL_SOURCES = {"traverse": ["k_bh.hip", "hts_lists.hpp", *_HEADERS],
+                  "items": ["k_bh.hip", "hts_lists.hpp", *_HEADERS],
+                  "attract": ["k_grad.hip", *_HEADERS],
+                  "tree": ["k_tree.hip", "k_sort.hip", *_HEADERS]}
 
 
 def _traffic(kernel, windows, setting):
