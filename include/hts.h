@@ -85,8 +85,10 @@ hts_status hts_check(hts_ctx ctx, hts_stream stream, uint32_t *bits_out);
  *  nnz_out    host: number of entries written, or needed on HTS_ECAPACITY.
  * The k-NN search is exact: squared distances are summed in double precision
  * over the dimensions in ascending order with fused multiply-adds.  The
- * bandwidth of row i solves perplexity(P_i) = perplexity in double precision
- * (bracketed from 1 by doubling or halving, at most 100 evaluations).
+ * bandwidth of row i solves perplexity(P_i) = perplexity in double precision:
+ * beta = 1 / (2 sigma^2) by Newton's steps from 4 / mean(D) (D: squared distances
+ * less the smallest) inside the bracket found so far, to a step below 1e-9 of beta,
+ * within 2^-100 <= beta <= 2^100.
  * ---------------------------------------------------------------------- */
 hts_status hts_build_affinities(hts_ctx ctx, hts_stream stream, const void *X,
                                 int64_t n, int32_t d, int32_t x_dtype,
@@ -317,8 +319,9 @@ hts_status hts_set_item_points(hts_ctx ctx, int32_t item_points);
 /* Size of the list that carries those short walks between the two kernels of
  * the traversal: each 64-query wave of the first kernel hands over at most
  * items_per_wave (>= 0) packets of them and makes the others itself.  A packet
- * is one walk or several small ones with one 64-lane partial force; the list is
- * sized for 552 bytes (1064 in double precision) per items_per_wave and wave
+ * is one walk or several small ones with one 64-lane partial force; a wave has room
+ * for 200 of them per 256 items_per_wave, rounded up, of 696 bytes each (1208 in
+ * double precision): 544 and 944 bytes per items_per_wave and wave at the default
  * (twice that for hts_gradient_hsne, whose two traversals run side by side).
  * The split depends only on the wave, so every setting gives the same result up
  * to the order of floating-point sums, and each setting gives it run after run;

@@ -37,7 +37,7 @@
 // large n and by the few workgroups at small n.  All of the above takes 12.0 ms
 // (0.11 and 0.05 ms): the two passes of products 3.8 ms each (7.6 when every tile
 // was formed for both of its blocks; n^2 d / 2 multiply-adds in half precision
-// at 1.0 PFLOP/s), the exact distances 3.7 ms (28 GB of candidates' rows, which
+// at 1.0 PFLOP/s), the exact distances 3.7 ms (25 GB of candidates' rows, which
 // come from beyond the L2).
 #include <climits>
 #include <cmath>
@@ -619,7 +619,7 @@ __device__ __forceinline__ void nearest(const double *sd, const int *sj, int m, 
 // 11 at n = 1000).  A query with a distance
 // that is not a number goes to the list of the direct kernel, which leaves such
 // candidates out.  Many points with many dimensions are bound by the rows, which
-// come from beyond the L2 at 6.9 TB/s (two pieces on their way made no
+// come from beyond the L2 at 6.7 TB/s (two pieces on their way made no
 // difference); the reverse neighbours are counted here because that hides the
 // additions to memory, 18 G/s, behind them.
 template <typename XT>
