@@ -312,8 +312,8 @@ hts_status hts_jobs_schedule(hts_ctx ctx, hts_stream stream, int32_t n_jobs,
  * Barnes-Hut walk hands every rejected cell of at most item_points points to
  * a separate short walk.  Results differ between settings only by the order
  * of floating-point sums.  Default 288, at which double-precision jobs of fewer
- * than 32768 points use a smaller size by their own number of points; applies
- * to later calls on ctx. */
+ * than 32768 points use a smaller size by their own number of points (but for
+ * cells whose leaves hold several points); applies to later calls on ctx. */
 hts_status hts_set_item_points(hts_ctx ctx, int32_t item_points);
 
 /* Size of the list that carries those short walks between the two kernels of
