@@ -322,7 +322,8 @@ hts_status hts_set_item_points(hts_ctx ctx, int32_t item_points);
  * is one walk or several small ones with one 64-lane partial force; a wave has room
  * for 200 of them per 256 items_per_wave, rounded up, of 696 bytes each (1208 in
  * double precision): 544 and 944 bytes per items_per_wave and wave at the default
- * (twice that for hts_gradient_hsne, whose two traversals run side by side).
+ * (twice that for hts_gradient_hsne, whose two traversals run side by side, or where
+ * one would take more than 32 GiB two of half the room).
  * The split depends only on the wave, so every setting gives the same result up
  * to the order of floating-point sums, and each setting gives it run after run;
  * smaller lists use less device memory and run slower once waves exceed their

@@ -35,6 +35,17 @@ __host__ __device__ inline Chunk chunk_of(int id0, int number, int q0, int start
 __host__ __device__ inline int64_t wave_cells(int id0) { return (int64_t)id0 * kCells; }
 __host__ __device__ inline int64_t chunk_cells(int id, int first) { return (int64_t)id * kCells + first; }
 
+// The list length of each of two traversals side by side, where one's workspace takes
+// `bytes` at the length asked for. Two of more than 32 GiB (3.9 million points in single
+// precision, 2.2 in double) get half the length each, which nearly halves them: a call
+// that fits a card with one workspace has to fit it with both (3 million points in double
+// precision 62 GB, as one after the other). Few waves hand over more: 3 million points 41.9
+// ms with whole and half lists, 17.3 and 17.4 in single precision.
+constexpr size_t kListsWhole = (size_t)32 << 30;
+__host__ __device__ inline int list_of_both(int list, size_t bytes) {
+    return bytes > kListsWhole ? (list < 256 ? list + 1 : 257) / 2 : list;
+}
+
 // The lists are kept in kGroups parts of entries(p) entries: take(p, i) for those
 // that taker w of `takers` takes.  own: each part has as many takers of its
 // own (own_parts(takers)), and w serves one part.  Else the parts' entries are dealt out one after another, on

@@ -1149,9 +1149,9 @@ struct BhLayout {
     size_t tot;
 };
 template <typename T>
-static BhLayout bh_layout(hts_ctx ctx, int64_t nqb, int64_t n, bool stats) {
+static BhLayout bh_layout(int list_items, int64_t nqb, int64_t n, bool stats) {
     const size_t nw = (size_t)nqb * kTopSlots;
-    const size_t share = chunks_of(ctx->list_items), chunks = nw * share;
+    const size_t share = chunks_of(list_items), chunks = nw * share;
     const size_t padded = (size_t)cdiv(nqb, kGroups) * kGroups * kTopSlots;  // waves, whole parts
     size_t sizes[BhLayout::R];
     sizes[BhLayout::Counts] = (size_t)kBhCounts * kCountStride * 4;
@@ -1176,7 +1176,7 @@ static BhLayout bh_layout(hts_ctx ctx, int64_t nqb, int64_t n, bool stats) {
 
 template <typename T>
 hts_status bh_item_counter(hts_ctx ctx, hts_tree t, int64_t n, unsigned **counter) {
-    const BhLayout L = bh_layout<T>(ctx, t->nqb, n, false);
+    const BhLayout L = bh_layout<T>(ctx->list_items, t->nqb, n, false);
     HTS_OKR(ensure(ctx->part, L.tot));
     *counter = (unsigned *)((char *)ctx->part.p + L.off[BhLayout::Counts]);
     return HTS_OK;
@@ -1186,11 +1186,11 @@ template hts_status bh_item_counter<double>(hts_ctx, hts_tree, int64_t, unsigned
 
 // the places of a traversal in its piece of the workspace
 template <typename T>
-static Walks<T> walks_at(char *base, const BhLayout &L, hts_ctx ctx, int64_t nqb, T *fattr,
+static Walks<T> walks_at(char *base, const BhLayout &L, int list_items, int64_t nqb, T *fattr,
                          uint64_t *stats) {
     const size_t *off = L.off;
     Walks<T> w;
-    w.ls.share = chunks_of(ctx->list_items);
+    w.ls.share = chunks_of(list_items);
     w.ls.part = cdiv(nqb, kGroups) * kTopSlots * w.ls.share;
     w.ls.count = (unsigned *)(base + off[BhLayout::Counts]);
     w.ls.chunks = (Chunk *)(base + off[BhLayout::Chunks]);
@@ -1276,9 +1276,9 @@ hts_status launch_bh_repulsion(hts_ctx ctx, hipStream_t st, hts_tree t, int64_t 
                                BhPrep<T> prep, PointRec<T> *pts, const int64_t *rp,
                                const int32_t *col, const T *val, T *fattr, double ex,
                                const double *ex_job, T *grad, double *z_dev, uint64_t *stats) {
-    const BhLayout L = bh_layout<T>(ctx, t->nqb, n, stats != nullptr);
+    const BhLayout L = bh_layout<T>(ctx->list_items, t->nqb, n, stats != nullptr);
     HTS_OKR(ensure(ctx->part, L.tot));
-    const Walks<T> w = walks_at<T>((char *)ctx->part.p, L, ctx, t->nqb, fattr, stats);
+    const Walks<T> w = walks_at<T>((char *)ctx->part.p, L, ctx->list_items, t->nqb, fattr, stats);
     if (prep.points || prep.thresholds || prep.clear) {
         // one thread per point, and the node thresholds strided over the same grid
         const int64_t gp = cdiv(n, kBlock) > 64 ? cdiv(n, kBlock) : 64;
@@ -1298,11 +1298,12 @@ template <typename T>
 hts_status launch_bh_hsne(hts_ctx ctx, hipStream_t st, hts_tree t, int64_t n, const T *Y, double theta,
                           PointRec<T> *pts, const int64_t *rp, const int32_t *col, const T *val, T *fattr,
                           T *fattr_euclid, double ex, double lambda, T *grad, double *z_dev, uint64_t *stats) {
-    const BhLayout L = bh_layout<T>(ctx, t->nqb, n, stats != nullptr);
+    const int list = list_of_both(ctx->list_items, bh_layout<T>(ctx->list_items, t->nqb, n, stats != nullptr).tot);
+    const BhLayout L = bh_layout<T>(list, t->nqb, n, stats != nullptr);
     HTS_OKR(ensure(ctx->part, 2 * L.tot));
     char *base = (char *)ctx->part.p;
-    const Walks<T> w = walks_at<T>(base, L, ctx, t->nqb, fattr, stats ? stats + 2 * kBhStats : nullptr);
-    const Walks<T> e = walks_at<T>(base + L.tot, L, ctx, t->nqb, fattr_euclid, stats);
+    const Walks<T> w = walks_at<T>(base, L, list, t->nqb, fattr, stats ? stats + 2 * kBhStats : nullptr);
+    const Walks<T> e = walks_at<T>(base + L.tot, L, list, t->nqb, fattr_euclid, stats);
     HTS_OKR(tree_euclid<T>(ctx, st, t, theta, EuclidExtras<T>{Y, pts, w.ls.count, e.ls.count}));
     if (stats)
         launch_walks<T, kBoth, true>(ctx, st, t, n, w, e, pts, rp, col, val, ex, nullptr, lambda, grad, z_dev);
